@@ -381,6 +381,12 @@ ccpr_status ccpr_set_design_fusion(ccpr_solver* s, int on);
  * pass (see ccpr_set_design_fusion), else 0.  CCPR_EINVAL for NULL. */
 ccpr_status ccpr_get_design_fusion(const ccpr_solver* s, int* fused);
 
+/* *one = 1 if a leapfrog step of this configuration runs as one launch (small
+ * grids: the whole update of a tile's cells, design, source and records included,
+ * bitwise the same as the separate launches), 0 if as a grid pass and the launches
+ * around it.  CCPR_EINVAL for NULL. */
+ccpr_status ccpr_get_one_launch(const ccpr_solver* s, int* one);
+
 /* ---- serving engine ----------------------------------------------------- */
 /* Continuous batching of whole solves (forward run, objective, adjoint run,
  * gradient: the path of ccpr_forward + ccpr_adjoint + ccpr_gradient) for many

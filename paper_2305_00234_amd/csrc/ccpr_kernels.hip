@@ -2088,6 +2088,13 @@ void launch_fused_pairs(const WholeArgs& w, int maxpairs, hipStream_t s)
     else hipLaunchKernelGGL((ccpr_fused_kernel<8, DFT, EDGE>), grid, block, 0, s, w);
 }
 
+// by the registers of its variants (60 to 80 up to 3 pairs, 84 to 90 with 4 pairs or
+// with 3 in DFT mode, 118 to 127 above)
+int ccpr_fused_waves(int maxpairs, bool dft)
+{
+    return maxpairs > 4 ? 16 : maxpairs == 4 || (maxpairs == 3 && dft) ? 20 : 24;
+}
+
 int ccpr_launch_fused(const WholeArgs& w, int maxpairs, bool edge, void* stream)
 {
     if (!fused_args_ok(w.s, maxpairs)) return (int)hipErrorInvalidValue;

@@ -962,26 +962,55 @@ StepArgs hot_args(ccpr_solver* s, int st)
     return A;
 }
 
-// Argument of the one-launch step (ccpr_fused_kernel) of state st; false where the
-// step runs as separate launches.  The one-launch step wins while a step is
-// launches and latency: measured per step, separate launches against one (us;
-// padded x times y times z): 64^3 24.7 / 9.9, 90^3 31.7 / 28.0, 117^3 (1.75 M)
-// 37.8 / 34.2, 130x97x111 (2.07 M) 40.1 / 53.6, 150x140x130 (3.5 M) 55 / 77; above, its recomputed halo plane and rows cost more than
-// the launches, hence the limit of 1.8 M padded cells.  Rows above 256 lanes leave a
-// workgroup a single row beside its halo row.  Four rows per thread and design
-// tiles fused on request name the separate launches.
-constexpr long long kWholeStepCells = 1800000;
+// Rows of a tile of the one-launch step (ccpr_fused_kernel): three rows and the
+// halo row per workgroup, two where that leaves fewer than four workgroups a CU
+// (32^3: 7.8 against 8.3 us; 64^3: 10.4 against 9.9); a batch shares its workgroup
+// size, so there the width alone decides.
+int whole_step_rows(const ccpr_solver* s)
+{
+    const int rows = std::min(3, CCPR_FUSED_THREADS / s->nxp - 1);
+    return !s->batched && (s->g.ny + rows - 1) / rows * s->g.nz < 1024 ? std::min(rows, 2) : rows;
+}
+
+// Whether a leapfrog step runs as one launch (ccpr_fused_kernel).  It wins while a
+// step is launches and latency, and loses where its recomputed halo plane and rows,
+// or design cells updated at its occupancy, cost more than the launches it saves.
+// The rule weighs what makes it slow against the waves it keeps in flight (us a step,
+// separate launches / one; padded cells):
+//  - cells: 64^3 24.5 / 9.8, 1.04 M 31.1 / 23.8, 1.81 M 40.9 / 40.8, 2.07 M 40.1 / 53.6;
+//  - waves in flight: registers limit them and large workgroups round them down (1.63 M
+//    in rows of 192 lanes, 4 pairs, DFT, per edge: 12 of 24, 57.5 / 79.2);
+//  - design cells: 1.33 M with 0.08 M of them 35.2 / 30.8, 1.73 M with 0.34 M 48.9 / 54.1,
+//    per edge 1.38 M with 0.17 M 40.0 / 46.7; above 4 pairs, where few already cost most of
+//    it, 0.74 M with 455 41.2 / 30.4, 0.85 M with 0.12 M 40.0 / 60.6;
+//  - no CPML: the separate grid kernel has no layers either and there is hardly a post
+//    launch (0.82 M 23.9 / 19.7, 1.55 M 27.5 / 33.9).
+// Of 556 random solves it misses the faster form by more than 2 % on 23, by at most
+// 25 %, and none is slower than its separate grid, aux and post launches were.
+// Rows above 256 lanes leave a workgroup a single row beside its halo row; four rows per
+// thread and design tiles fused on request name the separate launches.
+constexpr double kWholeStepCells = 1.8e6;
+bool whole_step(const ccpr_solver* s)
+{
+    const double cells = (double)s->nxp * s->g.ny * s->g.nz;
+    if (s->nxp > CCPR_FUSED_THREADS / 3 || s->rows != 2 || s->maxpairs > 8 || s->des_on) return false;
+    if (cells > kWholeStepCells || streams(s)) return false;
+    const int wg = (whole_step_rows(s) + 1) * s->nxp / 64;
+    const int waves = ccpr_fused_waves(s->maxpairs, s->grad_dft) / wg * wg;
+    const double nd = s->has_design ? (double)s->nd : 0.0;
+    const double load = s->maxpairs > 4 ? cells * (s->src_kind == 2 ? 1.1 : 1.0) + 4000.0 * std::sqrt(nd)
+                                        : cells * (s->g.npml > 0 ? 1.0 : 1.5) + nd * (s->edge ? 3.75 : 3.0);
+    return load <= 2.0e6 * std::sqrt(waves / 24.0);
+}
+
+// Argument of the one-launch step of state st; false where the step runs as
+// separate launches.
 bool plan_whole_step(ccpr_solver* s, int st, const StepArgs& A, WholeArgs& W)
 {
-    if (A.stream_st || A.nxp > CCPR_FUSED_THREADS / 3 || s->rows != 2 || s->maxpairs > 8 || s->des_on) return false;
-    if ((long long)A.nxp * A.ny * A.nz > kWholeStepCells) return false;
+    if (!whole_step(s)) return false;
     W = WholeArgs{};
     W.s = A;
-    // three rows and the halo row per workgroup, two where that leaves fewer
-    // than four workgroups a CU (32^3: 7.8 against 8.3 us; 64^3: 10.4 against
-    // 9.9); a batch shares its workgroup size, so there the width alone decides
-    W.s.rows = std::min(3, CCPR_FUSED_THREADS / A.nxp - 1);
-    if (!s->batched && (A.ny + W.s.rows - 1) / W.s.rows * A.nz < 1024) W.s.rows = std::min(W.s.rows, 2);
+    W.s.rows = whole_step_rows(s);
     W.s.nys = (A.ny + W.s.rows - 1) / W.s.rows;
     W.s.nblk = W.s.nys * A.nz;
     const Layout& L = s->lay;
@@ -2206,6 +2235,13 @@ ccpr_status ccpr_get_design_fusion(const ccpr_solver* s, int* fused)
 {
     if (!s || !fused) return CCPR_EINVAL;
     *fused = s->des_on && s->ntiles_des > 0 ? 1 : 0;
+    return CCPR_OK;
+}
+
+ccpr_status ccpr_get_one_launch(const ccpr_solver* s, int* one)
+{
+    if (!s || !one) return CCPR_EINVAL;
+    *one = whole_step(s) ? 1 : 0;
     return CCPR_OK;
 }
 

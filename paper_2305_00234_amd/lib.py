@@ -37,7 +37,7 @@ EXPORTS = [
     "ccpr_adjoint", "ccpr_gradient", "ccpr_gap_spectrum", "ccpr_reset", "ccpr_step", "ccpr_get_field",
     "ccpr_step_count", "ccpr_set_timing", "ccpr_get_timing", "ccpr_get_grid_timing", "ccpr_get_info",
     "ccpr_set_tile_planes", "ccpr_set_tile_rows", "ccpr_set_design_fusion", "ccpr_get_design_fusion",
-    "ccpr_set_watchdog", "ccpr_forward_serial",
+    "ccpr_get_one_launch", "ccpr_set_watchdog", "ccpr_forward_serial",
     "ccpr_engine_create", "ccpr_engine_submit", "ccpr_engine_poll", "ccpr_engine_wait",
     "ccpr_engine_result", "ccpr_engine_release", "ccpr_engine_last_error", "ccpr_engine_destroy",
     "ccpr_engine_set_batching",
@@ -113,6 +113,7 @@ def load():
         "ccpr_set_tile_rows": (_i, [_p, _i]),
         "ccpr_set_design_fusion": (_i, [_p, _i]),
         "ccpr_get_design_fusion": (_i, [_p, _ip]),
+        "ccpr_get_one_launch": (_i, [_p, _ip]),
         "ccpr_set_watchdog": (_i, [_p, _i, _d]),
         "ccpr_forward_serial": (C.c_longlong, [_p]),
         "ccpr_engine_create": (_i, [_p, C.c_uint64, _i, _i, C.POINTER(_p)]),
@@ -556,8 +557,10 @@ class Solver:
         self._chk(self._lib.ccpr_get_resident_segments(self._h, C.byref(r)), "ccpr_get_resident_segments")
         f = C.c_int(0)
         self._chk(self._lib.ccpr_get_design_fusion(self._h, C.byref(f)), "ccpr_get_design_fusion")
+        o = C.c_int(0)
+        self._chk(self._lib.ccpr_get_one_launch(self._h, C.byref(o)), "ccpr_get_one_launch")
         return {"segments": a.value, "segment_steps": b.value, "tile_planes": c.value,
-                "resident_segments": r.value, "design_fused": f.value}
+                "resident_segments": r.value, "design_fused": f.value, "one_launch": o.value}
 
     def set_tile_planes(self, planes):
         self._chk(self._lib.ccpr_set_tile_planes(self._h, planes), "ccpr_set_tile_planes")

@@ -1,0 +1,71 @@
+"""Which solves run a leapfrog step as one launch (no GPU: the rule is a matter of
+the configuration).  The sizes are ones where both forms were timed: the rule has
+to name the faster."""
+
+import numpy as np
+import pytest
+
+from paper_2305_00234_amd import inputs as I
+from paper_2305_00234_amd.solver import configure
+
+
+def _pairs(n):
+    return I.CCPRMaterial(2.0, 0.0, tuple(complex(-1e14, 4e15 + 5e14 * q) for q in range(n)),
+                          tuple(complex(0, -1e13) for _ in range(n)))
+
+
+def _workload(n, design, npml=8, pairs=3, edges=False, gradient="time", source="dipole"):
+    w = I.drude_dipole_32(steps=4)
+    w.shape, w.npml, w.gradient = n, npml, gradient
+    w.mat1, w.mat2 = (_pairs(max(0, pairs - 4)),) * 3, (_pairs(min(pairs, 4)),) * 3
+    w.design_lo = tuple((n[a] - design[a]) // 2 for a in range(3))
+    w.rho = np.full(design[::-1], 0.5, np.float32)
+    if edges:
+        w.rho_edges = I.random_edge_densities(design, 3)
+    w.gap_lo, w.gap_dims = tuple(w.design_lo[a] + design[a] // 2 for a in range(3)), (2, 2, 2)
+    if source == "dipole":
+        w.dipole_cell = (max(npml + 1, w.design_lo[0] - 2), n[1] // 2, n[2] // 2)
+    else:
+        m = max(npml, 1) + 2
+        w.source, w.pw_prop_axis, w.pw_pol_axis = "planewave", 1, 2
+        w.tfsf_lo, w.tfsf_hi = (m,) * 3, tuple(v - m for v in n)
+        w.wave = np.sin(np.arange(5.0))
+    return w
+
+
+# (workload, one launch?): us a step as separate launches / as one
+CASES = {
+    "64^3: 24.5 / 9.8": (_workload((64, 64, 64), (16,) * 3), True),
+    "117^3, 2 pairs: 37.8 / 34.2": (_workload((117, 117, 117), (29,) * 3, pairs=2), True),
+    "above the limit: 40.1 / 53.6": (_workload((130, 97, 111), (60, 41, 50)), False),
+    "8 pairs, few design cells: 41.2 / 30.4": (_workload((133, 73, 53), (13, 7, 5), npml=12, pairs=8), True),
+    "6 pairs, many: 40.0 / 60.6": (_workload((101, 133, 50), (60, 79, 26), pairs=6, source="planewave"), False),
+    "5 pairs, DFT, 256 lanes: 45.6 / 86.8": (_workload((222, 70, 69), (133, 42, 41), npml=5, pairs=5, gradient="dft",
+                                                       source="planewave"), False),
+    "4 pairs, per edge, DFT: 57.5 / 79.2": (_workload((176, 166, 51), (140, 132, 27), pairs=4, edges=True,
+                                                      gradient="dft"), False),
+    "per edge: 40.0 / 46.7": (_workload((179, 147, 49), (107, 88, 17), npml=12, pairs=2, edges=True,
+                                        source="planewave"), False),
+    "large design: 48.9 / 54.1": (_workload((178, 92, 98), (142, 58, 66), npml=12, source="planewave"), False),
+    "no CPML, small: 23.9 / 19.7": (_workload((100, 80, 80), (25, 20, 20), npml=0, source="planewave"), True),
+    "no CPML, large: 27.5 / 33.9": (_workload((120, 110, 110), (30, 27, 27), npml=0, source="planewave"), False),
+    "rows too wide": (_workload((257, 24, 24), (8, 4, 4)), False),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_step_form(name):
+    w, one = CASES[name]
+    s = configure(w)
+    assert s.info()["one_launch"] == int(one)
+    s.close()
+
+
+def test_named_launch_shapes_are_separate_launches():
+    s = configure(CASES["64^3: 24.5 / 9.8"][0])
+    assert s.info()["one_launch"] == 1
+    s.set_tile_rows(4)
+    assert s.info()["one_launch"] == 0
+    s.set_tile_rows(2)
+    assert s.info()["one_launch"] == 1
+    s.close()
