@@ -1191,9 +1191,11 @@ ccpr_status launch_step(ccpr_solver* s, StepArgs& A, int st, bool fuse)
     // step: 130x97x111 45.3 -> 40.3, 170x95x170 69.3 -> 67.4)
     // (per-edge designs need more registers, and from some size on more of them than the
     // joint kernel keeps in flight: 45 k cells 48.8 -> 46.8, 64 k 79.7 -> 77.6, 123 k
-    // 51.1 -> 51.3, 432 k 109 -> 122; per voxel 432 k 104 -> 100, 1.1 M 156 -> 150)
+    // 51.1 -> 51.3, 432 k 109 -> 122; per voxel 432 k 104 -> 100, 1.1 M 156 -> 150.
+    // Without a CPML there is no post work worth joining and the registers still cost:
+    // 126x272x106, 60 k cells 42.1 -> 43.4, 251x56x93, 88 k 26.6 -> 27.4)
     const bool tail = fuse && !fdes && ndes > 0 && !A.stream_st && s->maxpairs <= 4 && s->tail_ok[st] &&
-                      (!s->edge || ndes <= 100000);
+                      (!s->edge || (s->g.npml > 0 && ndes <= 100000));
     if (e == 0 && !fdes && !tail) e = ccpr_launch_aux(A, s->maxpairs, ndes, s->edge, As);
     const bool watch = s->watch_run && s->watch_every > 0 && s->has_obj && (A.n + 1) % s->watch_every == 0;
     // the next step of this state follows at once: its fork is this dispatch

@@ -69,3 +69,15 @@ def test_batched_solves_by_size_and_width():
     eng.close()
     for s in solvers:
         s.close()
+
+
+@pytest.mark.parametrize("edges", [False, True])
+def test_designs_without_layers(edges):
+    """No CPML: the joint launch per voxel, aux and post launches per edge."""
+    require_gpu()
+    w = _case((30, 27, 33), npml=0, edges=edges, lo=(1, 9, 9), design=(20, 6, 7), steps=40)
+    a, b = _solve(w, 2), _solve(w, 4)
+    say("no layers, edges", edges, "F", a[0])
+    assert a[0] == b[0]
+    for x, y in zip(a[1:], b[1:]):
+        assert np.array_equal(x, y)
