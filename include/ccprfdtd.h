@@ -353,12 +353,14 @@ ccpr_status ccpr_get_resident_segments(const ccpr_solver* s, int* resident);
 
 /* Launch shape: nominal z-planes per workgroup of the step kernel (default
  * 5; the planes are split into about nz/planes chunks of equal estimated
- * cost, so chunks in the CPML are thinner).  Results do not depend on it. */
+ * cost, so chunks in the CPML are thinner).  Setting it names the step kernel
+ * and the launches around it also where a step would run as one launch
+ * (ccpr_get_one_launch).  Results do not depend on it. */
 ccpr_status ccpr_set_tile_planes(ccpr_solver* s, int planes);
 
 /* Launch shape: y rows per thread of the step kernel, 2 (default) or 4
- * (4 only for nx <= 512: CCPR_ENOTSUP otherwise).  Results do not depend on
- * it. */
+ * (4 only for nx <= 512: CCPR_ENOTSUP otherwise).  4 names the step kernel as
+ * ccpr_set_tile_planes does.  Results do not depend on it. */
 ccpr_status ccpr_set_tile_rows(ccpr_solver* s, int rows);
 
 /* Launch shape: on = 1 lets the grid pass finish the design cells itself --

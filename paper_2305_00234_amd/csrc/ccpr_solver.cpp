@@ -987,13 +987,13 @@ int whole_step_rows(const ccpr_solver* s)
 //    launch (0.82 M 23.9 / 19.7, 1.55 M 27.5 / 33.9).
 // Of 556 random solves it misses the faster form by more than 2 % on 23, by at most
 // 25 %, and none is slower than its separate grid, aux and post launches were.
-// Rows above 256 lanes leave a workgroup a single row beside its halo row; four rows per
-// thread and design tiles fused on request name the separate launches.
+// Rows above 256 lanes leave a workgroup a single row beside its halo row; a tile height,
+// four rows per thread and design tiles fused on request name the separate launches.
 constexpr double kWholeStepCells = 1.8e6;
 bool whole_step(const ccpr_solver* s)
 {
     const double cells = (double)s->nxp * s->g.ny * s->g.nz;
-    if (s->nxp > CCPR_FUSED_THREADS / 3 || s->rows != 2 || s->maxpairs > 8 || s->des_on) return false;
+    if (s->nxp > CCPR_FUSED_THREADS / 3 || s->rows != 2 || s->tz_set || s->maxpairs > 8 || s->des_on) return false;
     if (cells > kWholeStepCells || streams(s)) return false;
     const int wg = (whole_step_rows(s) + 1) * s->nxp / 64;
     const int waves = ccpr_fused_waves(s->maxpairs, s->grad_dft) / wg * wg;

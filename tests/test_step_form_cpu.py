@@ -68,4 +68,6 @@ def test_named_launch_shapes_are_separate_launches():
     assert s.info()["one_launch"] == 0
     s.set_tile_rows(2)
     assert s.info()["one_launch"] == 1
+    s.set_tile_planes(5)
+    assert s.info()["one_launch"] == 0 and s.info()["tile_planes"] == 5
     s.close()
