@@ -1275,9 +1275,10 @@ ccpr_status forward_step(ccpr_solver* s, int n, int tslot, bool gap, bool fuse)
     StepArgs A = hot_args(s, 0);
     A.n = n;
     A.mode = gap && s->has_obj ? CCPR_MODE_GAP : 0;
-    if (s->grad_dft && s->lay.T) {
-        // DFT mode: T_hat += T^{n+1/2} exp(-j omega dt n) instead of the history
-        // (plain stepping, ccpr_step, has no gradient and its layout no T region)
+    if (s->grad_dft && gap) {
+        // DFT mode: T_hat += T^{n+1/2} exp(-j omega dt n) instead of the history, in
+        // forward runs only (plain stepping has no gradient: its layout has no T region,
+        // or still the smaller one of a forward run in the time-exact mode)
         const double ph = s->omega * s->dt * n;
         A.mode |= CCPR_MODE_DFT_T;
         A.phc = (float)std::cos(ph);

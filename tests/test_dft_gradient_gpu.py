@@ -127,3 +127,32 @@ def test_stepping_in_dft_mode_is_plain_stepping():
         s.close()
     assert np.abs(out[0]).max() > 0
     assert np.array_equal(out[0], out[1])
+
+
+def test_stepping_in_dft_mode_after_a_short_time_exact_run():
+    """Stepping after a forward run of two steps in the time-exact mode, whose history
+    is smaller than the transforms: nothing is accumulated, so the memory after the
+    workspace stays as it was and the fields are those of the time-exact mode."""
+    torch = require_gpu()
+    from paper_2305_00234_amd.solver import configure
+    out = []
+    for mode in ("time", "dft"):
+        w = I.drude_dipole_32(steps=40)
+        w.npml = 5
+        w.design_lo, w.rho = (6, 6, 6), np.random.default_rng(2).random((20, 20, 20)).astype(np.float32)
+        w.dipole_cell, w.gap_lo = (16, 16, 16), (12, 12, 12)
+        s = configure(w)
+        size, guard = s.workspace_size(2), 1 << 20
+        buf = torch.full((size + guard,), 0xA5, dtype=torch.uint8, device="cuda")
+        torch.cuda.synchronize()
+        s.bind_workspace(buf.data_ptr(), size)
+        s.forward(2)
+        s.set_gradient_mode(mode)
+        s.reset()
+        s.step(40)
+        out.append(np.stack([s.field(c) for c in range(6)]))
+        torch.cuda.synchronize()
+        assert bool((buf[size:] == 0xA5).all())
+        s.close()
+    assert np.abs(out[0]).max() > 0
+    assert np.array_equal(out[0], out[1])
