@@ -343,8 +343,10 @@ ccpr_status ccpr_get_timing(const ccpr_solver* s, double* step_ms_total, long lo
 ccpr_status ccpr_get_grid_timing(const ccpr_solver* s, double* grid_ms_total, long long* grid_launches);
 
 /* Segment count and length of the last ccpr_forward layout, and the number of
- * z-planes one workgroup of the step kernel marches over.  Any pointer may be
- * NULL. */
+ * z-planes one workgroup of the step kernel marches over: the nominal number
+ * (ccpr_set_tile_planes), more where a grid that fits the last-level cache is
+ * split into fewer chunks, 1 where a step runs as one launch
+ * (ccpr_get_one_launch).  Any pointer may be NULL. */
 ccpr_status ccpr_get_info(const ccpr_solver* s, int* segments, int* segment_steps, int* tile_planes);
 
 /* Resident segments of the last ccpr_forward layout (segments - resident of

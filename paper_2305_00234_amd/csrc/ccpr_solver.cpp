@@ -774,29 +774,41 @@ void fill_extra(const StepCold& C, std::vector<int4>& ex)
 // slower.)
 bool streams(const ccpr_solver* s) { return 48.0 * (double)s->npad > 256.0 * (1 << 20); }
 
-// z-chunks of the step kernel: about nz/tz chunks of equal estimated cost
-// (a plane in a z CPML layer also streams its psi memories: weight 1.6), so
-// that the XCDs, which each take an equal share of the chunks, finish
-// together.  Logical chunk q of XCD-contiguous order gets physical chunk
-// (q % 8) * (n/8) + q / 8 when n is a multiple of 8, which spreads the
-// expensive chunks over the XCDs.
+// Number of z-chunks of the step kernel: about nz/tz, a multiple of 8 where there
+// are that many.
+int nominal_chunks(const ccpr_solver* s)
+{
+    const int nz = s->g.nz, n = std::max(1, std::min(nz, (nz + s->tz - 1) / s->tz));
+    return n >= 8 && nz >= 8 * ((n + 7) / 8) ? (n + 7) / 8 * 8 : n;
+}
+int chunk_count(const ccpr_solver* s)
+{
+    const int n = nominal_chunks(s);
+    // One launch of cache-resident tiles: fewer chunks where the tiles are then all in
+    // flight at once (256 CUs, six waves a SIMD by the CPML kernel's registers) instead
+    // of leaving a second, nearly empty round (us a step, 32 / 24 chunks: 150x140x130
+    // 54.5 / 49.6, 190x150x150 84.8 / 75.4, 180x170x160 98.6 / 94.1); not by so much
+    // that the tiles grow past reason (16 chunks 52.8, 79.6, 99.6).  (Without a CPML the
+    // other variant runs, eight waves a SIMD: there 13 random sizes took 0.95 to 1.12
+    // times as long with the nominal count, 1.03 on average.)
+    if (!s->tz_set && !s->des_fuse && s->rows == 2 && !streams(s) && n % 8 == 0) {
+        const int fit = 256 * (24 / std::min(24, s->nxp / 64)) / ((s->g.ny + 1) / 2) / 8 * 8;
+        if (fit < n && 5 * fit >= 3 * n) return fit;
+    }
+    return n;
+}
+
+// z-chunks of the step kernel of equal estimated cost (a plane in a z CPML layer
+// also streams its psi memories: weight 1.6), so that the XCDs, which each take an
+// equal share of the chunks, finish together.  Logical chunk q of XCD-contiguous
+// order gets physical chunk (q % 8) * (n/8) + q / 8 when n is a multiple of 8, which
+// spreads the expensive chunks over the XCDs.
 #ifndef CCPR_ZPML_PLANE_COST
 #define CCPR_ZPML_PLANE_COST 1.6
 #endif
 void plan_chunks(ccpr_solver* s)
 {
-    const int nz = s->g.nz, np = s->g.npml;
-    int n = std::max(1, std::min(nz, (nz + s->tz - 1) / s->tz));
-    if (n >= 8 && nz >= 8 * ((n + 7) / 8)) n = (n + 7) / 8 * 8;
-    // One launch of cache-resident tiles: fewer chunks where the tiles are then all in
-    // flight at once (256 CUs, six waves a SIMD by the CPML kernel's registers) instead
-    // of leaving a second, nearly empty round (us a step, 32 / 24 chunks: 150x140x130
-    // 54.5 / 49.6, 190x150x150 84.8 / 75.4, 180x170x160 98.6 / 94.1); not by so much
-    // that the tiles grow past reason (16 chunks 52.8, 79.6, 99.6).
-    if (!s->tz_set && !s->des_fuse && s->rows == 2 && !streams(s) && n % 8 == 0) {
-        const int fit = 256 * (24 / std::min(24, s->nxp / 64)) / ((s->g.ny + 1) / 2) / 8 * 8;
-        if (fit < n && 5 * fit >= 3 * n) n = fit;
-    }
+    const int nz = s->g.nz, np = s->g.npml, n = chunk_count(s);
     std::vector<double> cum(nz + 1, 0.0);
     for (int k = 0; k < nz; ++k)
         cum[k + 1] = cum[k] + ((np > 0 && (k < np || k >= nz - np)) ? CCPR_ZPML_PLANE_COST : 1.0);
@@ -2190,7 +2202,10 @@ ccpr_status ccpr_get_info(const ccpr_solver* s, int* segments, int* segment_step
     if (!s) return CCPR_EINVAL;
     if (segments) *segments = s->lay.S;
     if (segment_steps) *segment_steps = s->lay.K;
-    if (tile_planes) *tile_planes = s->tz;
+    // the nominal height, unless the step is one launch (tiles of one plane) or the
+    // chunk rule made fewer, higher chunks
+    const int n = chunk_count(s);
+    if (tile_planes) *tile_planes = whole_step(s) ? 1 : n == nominal_chunks(s) ? s->tz : (s->g.nz + n - 1) / n;
     return CCPR_OK;
 }
 

@@ -71,3 +71,15 @@ def test_named_launch_shapes_are_separate_launches():
     s.set_tile_planes(5)
     assert s.info()["one_launch"] == 0 and s.info()["tile_planes"] == 5
     s.close()
+
+
+@pytest.mark.parametrize("n,planes", [((32, 32, 32), 1), ((320, 48, 48), 5), ((320, 320, 320), 5), ((150, 140, 130), 6),
+                                      ((190, 150, 150), 7), ((65, 30, 300), 1), ((130, 97, 111), 5)])
+def test_reported_tile_height(n, planes):
+    """1 for a one-launch step, the nominal 5, or that of the fewer chunks (24 of 130
+    and 150 planes) of a grid whose tiles then fit the chip at once."""
+    s = configure(_workload(n, (8, 8, 8)))
+    assert s.info()["tile_planes"] == planes
+    s.set_tile_planes(3)
+    assert s.info()["tile_planes"] == 3
+    s.close()
