@@ -108,6 +108,17 @@ def step_model_bytes(w):
     return 48 * nx * ny * nz + 32 * layer_cells + design_update_bytes(w)
 
 
+def timed_pass(w, info):
+    """(kernel, byte model) of what the solver's grid-pass timing measures: the
+    grid pass (with the design cells where it finishes them itself), or the whole
+    step where a step runs as one launch."""
+    if info.get("one_launch"):
+        return "ccpr_fused_kernel", step_model_bytes(w)
+    if info.get("design_fused"):
+        return "ccpr_step_kernel + ccpr_step_des_kernel", grid_model_bytes(w) + design_update_bytes(w)
+    return "ccpr_step_kernel", grid_model_bytes(w)
+
+
 def traffic_from_profile(kernel_src_hash, workload):
     """HBM bytes per launch from committed rocprofv3 counter summaries, if they
     were taken on the current kernel source and this workload; else None."""
@@ -304,8 +315,8 @@ def other_workload(name):
             "step_frac": round(step_model_bytes(w) / step_s / 1e9 / HBM_PEAK_GBS, 4),
             "grid_pass_us": round(pass_s * 1e6, 2),
             "design_update_in_grid_pass": bool(info.get("design_fused")),
-            "grid_frac": round((grid_model_bytes(w) + (design_update_bytes(w) if info.get("design_fused") else 0))
-                               / pass_s / 1e9 / HBM_PEAK_GBS, 4)}
+            "one_launch_step": bool(info.get("one_launch")),
+            "grid_frac": round(timed_pass(w, info)[1] / pass_s / 1e9 / HBM_PEAK_GBS, 4)}
 
 
 def copy_rate_gbs(nbytes=1 << 30, reps=10):
@@ -437,9 +448,8 @@ def main():
     value = updates / (total / args.steps) / 1e6
     avg_step_s = step_ms / 1e3 / max(launches, 1)
     avg_launch_s = grid_ms / 1e3 / max(grid_launches, 1)
-    # with the design update inside the grid pass its bytes belong to the pass
     fused = bool(info.get("design_fused"))
-    alg = grid_model_bytes(w) + (design_update_bytes(w) if fused else 0)
+    kernel, alg = timed_pass(w, info)
     achieved = alg / avg_launch_s / 1e9
     sb = step_model_bytes(w)
     traffic = traffic_from_profile(kernel_hash(), w.name)
@@ -471,7 +481,7 @@ def main():
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": traffic,
-                     "kernel": "ccpr_step_kernel + ccpr_step_des_kernel" if fused else "ccpr_step_kernel",
+                     "kernel": kernel,
                      "design_update_in_grid_pass": fused,
                      "grid_model_bytes": int(alg),
                      "avg_launch_us": round(avg_launch_s * 1e6, 2), "launches": grid_launches,

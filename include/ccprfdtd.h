@@ -323,8 +323,8 @@ int ccpr_step_count(const ccpr_solver* s);
 /* Enable (1) or disable (0) stream-event timing of the leapfrog loops of
  * ccpr_forward and ccpr_adjoint, and clear the counters.  Timing records HIP
  * events on the bound stream around each loop and around every launch of the
- * grid kernel (the one that streams all cells), and synchronises the stream
- * at the end of each loop.  enable = k > 1 times only every k-th grid pass
+ * grid kernel (the one that streams all cells; the step's one launch where it
+ * runs as one), and synchronises the stream at the end of each loop.  enable = k > 1 times only every k-th grid pass
  * (the loops are still timed whole): fewer events in the stream, the same
  * average pass duration.  CCPR_EINVAL if negative. */
 ccpr_status ccpr_set_timing(ccpr_solver* s, int enable);
@@ -339,7 +339,11 @@ ccpr_status ccpr_get_timing(const ccpr_solver* s, double* step_ms_total, long lo
  * one launch of the grid kernel, or two concurrent launches (CPML tiles on
  * the bound stream, interior tiles on a second stream); it is timed from an
  * event on the bound stream before the first launch to the later of the
- * events recorded after each launch on its own stream. */
+ * events recorded after each launch on its own stream.  Where a step runs as one
+ * launch (ccpr_get_one_launch) there is no separate grid pass: the time and
+ * number are those of the steps, whose launch also updates the design, x-layer
+ * and source cells and writes the records; ccpr_set_tile_planes names the
+ * separate grid pass. */
 ccpr_status ccpr_get_grid_timing(const ccpr_solver* s, double* grid_ms_total, long long* grid_launches);
 
 /* Segment count and length of the last ccpr_forward layout, and the number of

@@ -543,7 +543,8 @@ class Solver:
         return ms.value, n.value
 
     def grid_timing(self):
-        """(total ms, launches) of the grid kernel inside the timed loops."""
+        """(total ms, launches) of the grid kernel inside the timed loops, or of the
+        whole step where it runs as one launch (info()["one_launch"])."""
         ms = C.c_double(0.0)
         n = C.c_longlong(0)
         self._chk(self._lib.ccpr_get_grid_timing(self._h, C.byref(ms), C.byref(n)), "ccpr_get_grid_timing")

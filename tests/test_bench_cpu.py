@@ -31,3 +31,16 @@ def test_byte_model_of_the_320_cube_workload():
     assert pairs == 9
     step = 48 * cells + 32 * (3 * 2 * p * n * n) + (16 * pairs + 4 + 28) * nd
     assert bench.step_model_bytes(w) == step == 2169241600
+
+
+def test_timed_pass_of_a_one_launch_step_is_the_whole_step():
+    """The grid-pass timing of a solve whose step is one launch measures that launch:
+    its byte model is the step's, not the grid pass's."""
+    sys.path.insert(0, ROOT)
+    import bench
+    w = bench.workload_by_name("gold_gap_320", 10)
+    assert bench.timed_pass(w, {"one_launch": 0, "design_fused": 0}) == ("ccpr_step_kernel", 1730150400)
+    assert bench.timed_pass(w, {"one_launch": 1, "design_fused": 0}) == ("ccpr_fused_kernel", 2169241600)
+    kernel, nbytes = bench.timed_pass(w, {"one_launch": 0, "design_fused": 1})
+    assert kernel == "ccpr_step_kernel + ccpr_step_des_kernel"
+    assert nbytes == 1730150400 + bench.design_update_bytes(w)
