@@ -22,7 +22,7 @@
 // centres: x edges at (i+1/2, j, k), y edges at (i, j+1/2, k), z edges at
 // (i, j, k+1/2) of an N-cell design, component c holding N_l + 1 - delta(c,l)
 // edges along axis l; flat arrays hold the x, y, z edges in turn, each x
-// fastest) use the same kernel: Eq. FilterFunction's sphere around an edge
+// fastest) use the same kernels: Eq. FilterFunction's sphere around an edge
 // takes in the edges of all three components, and between component b and the
 // output's component a the index offset o maps to the distance |o + h_b - h_a|,
 // h_c the half-cell vector along axis c (|o| < R + 1/2).  One launch covers the
@@ -358,12 +358,14 @@ __global__ __launch_bounds__(256) void filter_project_grad_kernel(const double* 
 constexpr int kFT = 16;                // output tile edge (x and y)
 constexpr int kMaxRi = 16;             // largest integer offset (radius <= 17)
 constexpr int kTW = kFT + 2 * kMaxRi;  // staged tile edge
+constexpr int kMaxH = 17;              // per edge: |offset| < radius + 1/2
+constexpr int kTWE = kFT + 2 * kMaxH;
 
-// The same on small voxel grids, one output a thread: a workgroup owns a 16 x 16
-// tile of one output plane; for every z offset it stages the input plane's tile
-// plus an R-wide halo as (value, inside) pairs, with the cone weights of that
-// offset's disk, and each lane sums the disk straight from LDS (three LDS words
-// for two FMAs, but four times the waves; see voxels_small).
+// The same per voxel with one output a thread: a workgroup owns a 16 x 16 tile of
+// one output plane; for every z offset it stages the input plane's tile plus an
+// R-wide halo as (value, inside) pairs, with the cone weights of that offset's
+// disk, and each lane sums the disk straight from LDS (three LDS words for two
+// FMAs, but four times the waves; see one_output).
 __global__ __launch_bounds__(256) void voxel_filter_kernel(const float* __restrict__ rho, float* rho_t,
                                                              float* rho_b, float* wsum, int nx, int ny, int nz,
                                                              float R, int Ri, float beta, float eta, float tbe,
@@ -459,6 +461,122 @@ __global__ __launch_bounds__(256) void voxel_filter_grad_kernel(const double* __
         }
     }
     if (i < nx && j < ny) g[((long long)k * ny + j) * nx + i] = acc;
+}
+
+// Per edge with one output a thread, where 32 x 32 tiles stay mostly empty or the
+// sphere holds few taps (one_output); one launch per output component.  Per input
+// component: the sum over its taps around the output tile; 'stage'
+// fills the tile (one LDS word per position, zero outside b's edges) and
+// 'tap' consumes one staged word with its weight.  Offsets and weights are
+// uniform across the workgroup: each z offset's cone weights (zero outside
+// the sphere) are tabulated once in LDS (wts, (2H+1)^2 words) while the
+// tile is staged, so a tap costs two LDS reads and the accumulation.
+template <typename Stage, typename Tap>
+__device__ __forceinline__ void edge_taps(int a, int b, const FilterGeom& g, int k, float R, float R2, int H,
+                                          float* wts, Stage stage, Tap tap)
+{
+    const int tx = threadIdx.x % kFT, ty = threadIdx.x / kFT;
+    const float sx = 0.5f * ((b == 0) - (a == 0)), sy = 0.5f * ((b == 1) - (a == 1)),
+                sz = 0.5f * ((b == 2) - (a == 2));
+    const int W = kFT + 2 * H, D = 2 * H + 1;
+    for (int dz = -H; dz <= H; ++dz) {
+        const int kk = k + dz;
+        const float fz = (float)dz + sz;
+        const float rz2 = R2 - fz * fz;
+        if (kk < 0 || kk >= g.shp[b][2] || rz2 <= 0.f) continue;  // uniform
+        __syncthreads();
+        stage(kk, W);
+        for (int t = threadIdx.x; t < D * D; t += blockDim.x) {
+            const int qy = t / D, qx = t - qy * D;
+            const float fx = (float)(qx - H) + sx, fy = (float)(qy - H) + sy;
+            const float d2 = fx * fx + fy * fy + fz * fz;
+            wts[t] = d2 < R2 ? R - sqrtf(d2) : 0.f;
+        }
+        __syncthreads();
+        for (int dy = -H; dy <= H; ++dy) {
+            const float fy = (float)dy + sy;
+            const float ry2 = rz2 - fy * fy;
+            if (ry2 <= 0.f) continue;  // uniform
+            const float rr = sqrtf(ry2);
+            const int dxl = max(-H, (int)floorf(-sx - rr)), dxh = min(H, (int)ceilf(-sx + rr));
+            const int rowb = (ty + H + dy) * W + (tx + H);
+            const float* wrow = wts + (dy + H) * D + H;
+            for (int dx = dxl; dx <= dxh; ++dx) tap(rowb + dx, wrow[dx]);  // zero weight outside the sphere
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) void edge_filter_project_kernel(const float* __restrict__ rho, float* rho_t,
+                                                                  float* rho_b, float* wsum, const FilterGeom g,
+                                                                  int a, float R, float R2, int H, float beta,
+                                                                  float eta, float tbe, float inv_den)
+{
+    __shared__ float2 tile[kTWE * kTWE];  // (density, 1) on an edge of b, (0, 0) elsewhere
+    __shared__ float wts[(2 * kMaxH + 1) * (2 * kMaxH + 1)];
+    const int tx = threadIdx.x % kFT, ty = threadIdx.x / kFT;
+    const int i = blockIdx.x * kFT + tx, j = blockIdx.y * kFT + ty, k = blockIdx.z;
+    const int gx0 = blockIdx.x * kFT - H, gy0 = blockIdx.y * kFT - H;
+    float num = 0.f, den = 0.f;
+    for (int b = 0; b < 3; ++b) {
+        const int bx = g.shp[b][0], by = g.shp[b][1];
+        const float* src = rho + g.off[b];
+        auto stage = [&](int kk, int W) {
+            for (int t = threadIdx.x; t < W * W; t += blockDim.x) {
+                const int ly = t / W, lx = t - ly * W;
+                const int gx = gx0 + lx, gy = gy0 + ly;
+                const bool in = gx >= 0 && gx < bx && gy >= 0 && gy < by;
+                tile[t] = in ? make_float2(src[((long long)kk * by + gy) * bx + gx], 1.f) : make_float2(0.f, 0.f);
+            }
+        };
+        auto tap = [&](int idx, float w) {
+            const float2 v = tile[idx];
+            num = fmaf(w, v.x, num);
+            den = fmaf(w, v.y, den);
+        };
+        edge_taps(a, b, g, k, R, R2, H, wts, stage, tap);
+    }
+    if (i < g.shp[a][0] && j < g.shp[a][1]) {
+        const long long n = g.off[a] + ((long long)k * g.shp[a][1] + j) * g.shp[a][0] + i;
+        const float rt = num / den;
+        rho_t[n] = rt;
+        wsum[n] = den;
+        rho_b[n] = (tbe + tanhf(beta * (rt - eta))) * inv_den;
+    }
+}
+
+__global__ __launch_bounds__(256) void edge_filter_project_grad_kernel(const double* __restrict__ g_b,
+                                                                       const float* __restrict__ rho_t,
+                                                                       const float* __restrict__ wsum, double* gout,
+                                                                       const FilterGeom g, int a, float R, float R2,
+                                                                       int H, double beta, double eta,
+                                                                       double inv_den)
+{
+    __shared__ double tile[kTWE * kTWE];  // v = dF/drho_b * drho_b/drho_t / W on an edge of b, 0 elsewhere
+    __shared__ float wts[(2 * kMaxH + 1) * (2 * kMaxH + 1)];
+    const int tx = threadIdx.x % kFT, ty = threadIdx.x / kFT;
+    const int i = blockIdx.x * kFT + tx, j = blockIdx.y * kFT + ty, k = blockIdx.z;
+    const int gx0 = blockIdx.x * kFT - H, gy0 = blockIdx.y * kFT - H;
+    double acc = 0.0;
+    for (int b = 0; b < 3; ++b) {
+        const int bx = g.shp[b][0], by = g.shp[b][1];
+        const long long ob = g.off[b];
+        auto stage = [&](int kk, int W) {
+            for (int t = threadIdx.x; t < W * W; t += blockDim.x) {
+                const int ly = t / W, lx = t - ly * W;
+                const int gx = gx0 + lx, gy = gy0 + ly;
+                double v = 0.0;
+                if (gx >= 0 && gx < bx && gy >= 0 && gy < by) {
+                    const long long m = ob + ((long long)kk * by + gy) * bx + gx;
+                    const double th = tanh(beta * ((double)rho_t[m] - eta));
+                    v = g_b[m] * (beta * (1.0 - th * th) * inv_den) / (double)wsum[m];
+                }
+                tile[t] = v;
+            }
+        };
+        auto tap = [&](int idx, float w) { acc = fma((double)w, tile[idx], acc); };
+        edge_taps(a, b, g, k, R, R2, H, wts, stage, tap);
+    }
+    if (i < g.shp[a][0] && j < g.shp[a][1]) gout[g.off[a] + ((long long)k * g.shp[a][1] + j) * g.shp[a][0] + i] = acc;
 }
 
 // Eq. MeasureOfNon-discretness: one workgroup, fixed summation order (lanes,
@@ -583,23 +701,51 @@ void launch_filter_grad(const double* g_b, const float* rho_t, const float* wsum
                        wsum, g, L.g, R, R2, beta, eta, 1.0 / den);
 }
 
-// 32 x 32 tiles of all output planes.
-long long filter_tiles(const int* d, bool edges)
+// Tiles of e x e outputs of all output planes.
+long long filter_tiles(const int* d, bool edges, int e = 32)
 {
-    const int e = edges ? 1 : 0;
-    return (long long)((d[0] + e + 31) / 32) * ((d[1] + e + 31) / 32) * (edges ? 3LL * d[2] + 2 : d[2]);
+    const int x = d[0] + (edges ? 1 : 0), y = d[1] + (edges ? 1 : 0);
+    return (long long)((x + e - 1) / e) * ((y + e - 1) / e) * (edges ? 3LL * d[2] + 2 : d[2]);
 }
 
-// Voxel grids too small to fill the chip with 32 x 32 tiles keep one output a
-// thread (us, new / that): forward 24^3 at R = 5 56 / 35, 33x65x31 at 4.3 50 / 33,
-// 100x25x100 (400 tiles) at 3 and 7.5 38 / 24 and 167 / 169, 160x160x80 (2000) at 6
-// 173 / 431; chain rule 24^3 55 / 45, 33x65x31 (186) 58 / 55, 100x25x100 34 / 45 and
-// 185 / 302, 160x160x80 327 / 850.  (Per edge the new kernel wins at every size:
-// 24^3 at R = 2 52 / 71, at R = 5 221 / 447; 130x33x77 at R = 1 50 / 57.)
-// So do radii up to 1, where a voxel has only itself to read (forward 300x300x40 42 / 21).
-bool voxels_small(const int* d, double radius, bool grad)
+// Whether one output a thread in 16 x 16 tiles is faster than 4 or 8 in 32 x 32 ones.
+// Those need enough tiles to fill the chip, tiles that are not mostly empty (q: 16 x 16
+// tiles of the outputs per 32 x 32 tile, 4 where all are full) and a sphere large
+// enough that the taps and not the staging are the work.  Timed on 520 grids a
+// kernel (us, one output / several):
+//  - voxels forward: too few tiles 100x25x100 R 3 24 / 38, 33x65x31 R 4.3 33 / 50; empty
+//    10x10x2000 (q 1) R 5 0.74 to 1, 14x200x300 (1.9) R 3 / 4 0.93, 1.02; small spheres
+//    48x48x800 (2.25) R 2 / 3 0.77, 1.01, 300x300x40 (3.6) R 1.2 / 2 1.00, 1.17, all of
+//    them R 1 (a voxel reads only itself: 300x300x40 21 / 42);
+//  - voxels chain rule: 24^3 45 / 55 but 100x25x100 R 3 45 / 34; 16x16x1000 (1) 0.82,
+//    14x100x100 (1.75) R 3 0.85, 33x33x1000 (2.25) R 2 / 3 0.99, 1.20;
+//  - per edge, where three components share the staging, only empty tiles and the
+//    smallest spheres: forward 8x8x1200 (1) R 3 180 / 257, 10x10x300 1.30, 14x200x300 R
+//    1.5 / 2 0.82, 1.03, 33x33x1000 R 1.5 0.92; chain rule 8x8x1200 262 / 396, 14x100x100
+//    R 1.5 / 2 0.82, 1.06, 200x10x100 1.11.
+bool one_output(const int* d, double radius, bool edges, bool grad)
 {
-    return radius <= 1.0 || filter_tiles(d, false) < (grad ? 300 : 1024);
+    const long long tiles = filter_tiles(d, edges), full = filter_tiles(d, edges, kFT);
+    const double q = (double)full / (double)tiles;
+    if (!edges && radius <= 1.0) return true;
+    if (d[1] >= 65535 * kFT) return false;  // (rows beyond the 16 x 16 tiles' grid)
+    if (edges) {
+        const int x = d[0] + 1;  // a half-empty last tile along x only: 1 to 1.5
+        const bool narrow = 2 * ((x + kFT - 1) / kFT) <= 3 * ((x + 31) / 32);
+        if (q < 1.5) return (double)tiles >= (!grad && radius < 1.75 ? 700.0 : 1000.0 + 250.0 * radius);
+        if (grad) return radius < 1.75 && tiles >= 1024 && q < 2.4 && narrow;
+        return radius < (x <= kFT ? 2.25 : 1.75) && tiles >= 800 && q < 2.6;
+    }
+    if (grad) return tiles < 300 || q < 1.75 || (q < 2.5 && full < 1300) || (radius <= 2.0 && q >= 2.0 && q < 2.5);
+    if (tiles < 1024 || q < 1.75) return true;
+    if (radius <= 2.0) return radius < 1.3 || q < 3.0 || tiles < 1800;
+    return full < (radius <= 3.0 ? 4500 : radius <= 5.0 ? 3800 : 2500);
+}
+
+// Grid of 16 x 16 output tiles of every plane.
+dim3 tiles16(const int* d)
+{
+    return dim3((unsigned)((d[0] + kFT - 1) / kFT), (unsigned)((d[1] + kFT - 1) / kFT), (unsigned)d[2]);
 }
 
 // 8 outputs a thread and two waves a workgroup where the tiles fill the chip,
@@ -610,16 +756,24 @@ ccpr_status run_filter(const float* rho, float* rho_t, float* rho_b, float* wsum
                        double beta, double eta, void* hip_stream)
 {
     hipStream_t s = (hipStream_t)hip_stream;
-    if (!EDGE && voxels_small(dims, radius, false)) {
+    if (one_output(dims, radius, EDGE, false)) {
         const double den = std::tanh(beta * eta) + std::tanh(beta * (1.0 - eta));
-        dim3 grid((unsigned)((dims[0] + kFT - 1) / kFT), (unsigned)((dims[1] + kFT - 1) / kFT), (unsigned)dims[2]);
-        hipLaunchKernelGGL(voxel_filter_kernel, grid, dim3(kFT * kFT), 0, s, rho, rho_t, rho_b, wsum, dims[0], dims[1],
-                           dims[2], (float)radius, radius_to_offsets(radius), (float)beta, (float)eta,
-                           (float)std::tanh(beta * eta), (float)(1.0 / den));
-    } else if (filter_tiles(dims, EDGE) >= 1024) {
+        const float R = (float)radius, b = (float)beta, e = (float)eta, tbe = (float)std::tanh(beta * eta),
+                    inv = (float)(1.0 / den);
+        if constexpr (EDGE) {
+            const int H = (int)std::ceil(radius);
+            const FilterGeom g = plan_filter(dims, true, H, 1, 1, sizeof(float), kFT * kFT).g;
+            for (int a = 0; a < 3; ++a)
+                hipLaunchKernelGGL(edge_filter_project_kernel, tiles16(g.shp[a]), dim3(kFT * kFT), 0, s, rho, rho_t, rho_b,
+                                   wsum, g, a, R, (float)(radius * radius), H, b, e, tbe, inv);
+        } else {
+            hipLaunchKernelGGL(voxel_filter_kernel, tiles16(dims), dim3(kFT * kFT), 0, s, rho, rho_t, rho_b, wsum,
+                               dims[0], dims[1], dims[2], R, radius_to_offsets(radius), b, e, tbe, inv);
+        }
+    } else if (!EDGE || filter_tiles(dims, EDGE) >= 1024) {
         launch_filter<8, EDGE>(rho, rho_t, rho_b, wsum, dims, radius, beta, eta, 128, s);
-    } else {
-        launch_filter<4, EDGE>(rho, rho_t, rho_b, wsum, dims, radius, beta, eta, 256, s);
+    } else if constexpr (EDGE) {
+        launch_filter<4, true>(rho, rho_t, rho_b, wsum, dims, radius, beta, eta, 256, s);
     }
     return hipGetLastError() == hipSuccess ? CCPR_OK : CCPR_EDEVICE;
 }
@@ -632,11 +786,19 @@ ccpr_status run_filter_grad(const double* g_b, const float* rho_t, const float* 
 {
     hipStream_t s = (hipStream_t)hip_stream;
     const long long tiles = filter_tiles(dims, EDGE);
-    if (!EDGE && voxels_small(dims, radius, true)) {
-        const double den = std::tanh(beta * eta) + std::tanh(beta * (1.0 - eta));
-        dim3 grid((unsigned)((dims[0] + kFT - 1) / kFT), (unsigned)((dims[1] + kFT - 1) / kFT), (unsigned)dims[2]);
-        hipLaunchKernelGGL(voxel_filter_grad_kernel, grid, dim3(kFT * kFT), 0, s, g_b, rho_t, wsum, g, dims[0], dims[1],
-                           dims[2], (float)radius, radius_to_offsets(radius), beta, eta, 1.0 / den);
+    if (one_output(dims, radius, EDGE, true)) {
+        const double inv = 1.0 / (std::tanh(beta * eta) + std::tanh(beta * (1.0 - eta)));
+        const float R = (float)radius;
+        if constexpr (EDGE) {
+            const int H = (int)std::ceil(radius);
+            const FilterGeom geo = plan_filter(dims, true, H, 1, 1, sizeof(double), kFT * kFT).g;
+            for (int a = 0; a < 3; ++a)
+                hipLaunchKernelGGL(edge_filter_project_grad_kernel, tiles16(geo.shp[a]), dim3(kFT * kFT), 0, s, g_b, rho_t,
+                                   wsum, g, geo, a, R, (float)(radius * radius), H, beta, eta, inv);
+        } else {
+            hipLaunchKernelGGL(voxel_filter_grad_kernel, tiles16(dims), dim3(kFT * kFT), 0, s, g_b, rho_t, wsum, g,
+                               dims[0], dims[1], dims[2], R, radius_to_offsets(radius), beta, eta, inv);
+        }
     } else if (tiles >= 1536) {
         launch_filter_grad<8, 2, EDGE>(g_b, rho_t, wsum, g, dims, radius, beta, eta, 128, s);
     } else if (tiles >= 1024) {
