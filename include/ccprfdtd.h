@@ -402,9 +402,9 @@ ccpr_status ccpr_get_one_launch(const ccpr_solver* s, int* one);
  * arena and a worker thread: it admits submitted solves in arrival order
  * while the arena (first fit) and the slot limit allow and binds each to its
  * own slice of the arena.  Solves with one density per voxel, the time-exact
- * gradient and up to 1.8 M padded cells are batched: those of one padded x width
+ * gradient and up to 0.2 M padded cells are batched: those of one padded x width
  * (nx rounded up to 64) share a HIP stream, and each batched launch (the whole
- * step in one, or the grid, aux and post work where rows exceed 256 cells)
+ * step in one, or the grid, aux and post work where a step is not one launch)
  * advances up to 8 of them by one leapfrog step (a table in the launch maps
  * workgroups to solves); their other work (checkpoints, objective, results)
  * is enqueued per solve on the same stream in order.  Other solves get HIP

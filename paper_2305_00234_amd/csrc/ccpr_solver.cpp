@@ -2414,15 +2414,19 @@ long long ccpr_pipe_design_voxels(const ccpr_solver* s) { return s->has_design ?
 
 static_assert(CCPR_PIPE_BATCH_MAX == CCPR_BATCH_MAX, "batch sizes of the engine and the kernels differ");
 
+// Batched steps save launches where a step is little else; above, one stream's steps
+// leave the device idle between them and a solve's own launches overlap other solves'
+// better (16 requests, 8 active, batched against own streams, ms; sides, padded cells):
+// 20-32 (0.05 M) 33 / 51, 32-44 (0.1 M) 42 / 47, 44-56 (0.2 M) 54 / 55, 56-64 72 / 65,
+// 72-84 134 / 102, 100-117 227 / 176; without a CPML 56-64 59 / 58, 84-100 138 / 111.
+constexpr double kBatchCells = 0.2e6;
+
 int ccpr_pipe_batch_class(const ccpr_solver* s)
 {
     // batched launches cover one density per voxel, the time-exact gradient,
     // 2 rows per thread and x layers that fit the fused post kernel's blocks
     if (s->edge || s->grad_dft || s->rows != 2 || 2 * s->g.npml > 256) return -1;
-    // above the one-launch step's limit a solve's own launches (grid, tail) fill the
-    // device and overlap across streams better than batched grid, aux and post
-    // launches (24 requests on 64^3 to 192^3 grids: 3.99 -> 4.19 solves/s)
-    if ((long long)s->nxp * s->g.ny * s->g.nz > kWholeStepCells) return -1;
+    if ((double)s->nxp * s->g.ny * s->g.nz > kBatchCells) return -1;
     return s->nxp;
 }
 

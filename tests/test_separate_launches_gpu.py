@@ -10,7 +10,7 @@ from paper_2305_00234_amd import inputs as I
 from tests.gpu_util import (field_errors, gpu_fields_after_steps, gpu_gradient, oracle_fields_after_steps, oracle_gradient,
                             rel_l2, require_gpu, say)
 from tests.test_random_configs_gpu import PW_SEEDS, random_case, random_planewave_case
-from tests.test_whole_step_gpu import CASES
+from tests.test_whole_step_gpu import CASES, _case
 
 pytestmark = pytest.mark.gpu
 
@@ -117,6 +117,31 @@ def test_named_tile_height_in_a_served_batch():
     solvers[1].set_tile_planes(5)
     eng = Engine(1 << 30, max_active=3, chunk_steps=8)
     tickets = [eng.submit(s, CASES[n].steps) for s, n in zip(solvers, names)]
+    for t, a in zip(tickets, alone):
+        assert eng.wait(t) == JOB_DONE
+        F, g, _ = eng.result(t)
+        assert F == a[0] and np.array_equal(_flat(g), a[3])
+        eng.release(t)
+    eng.close()
+    for s in solvers:
+        s.close()
+
+
+def test_served_solves_on_both_sides_of_the_batching_line():
+    """0.2 M padded cells: rows too wide for the one-launch step batched as grid, aux and
+    post launches (three of one width), small one-launch solves batched, and solves just
+    above the line on streams of their own; bitwise their results alone."""
+    require_gpu()
+    from paper_2305_00234_amd.lib import JOB_DONE, Engine
+    from paper_2305_00234_amd.solver import configure
+    ws = [_case((270, 25, 24), steps=20), _case((290, 24, 25), steps=24), _case((264, 20, 30), npml=4, steps=22),
+          _case((300, 26, 25), steps=18), _case((60, 55, 56), steps=26), _case((60, 56, 56), steps=20),
+          _case((62, 57, 56), mats=2, steps=20), _case((64, 64, 64), npml=0, steps=20)]
+    alone = [_solve(w) for w in ws]
+    assert [a[4] for a in alone] == [0, 0, 0, 0, 1, 1, 1, 1]
+    solvers = [configure(w) for w in ws]
+    eng = Engine(2 << 30, max_active=8, chunk_steps=8)
+    tickets = [eng.submit(s, w.steps) for s, w in zip(solvers, ws)]
     for t, a in zip(tickets, alone):
         assert eng.wait(t) == JOB_DONE
         F, g, _ = eng.result(t)
