@@ -3,12 +3,12 @@
 // The caller hands over one device arena (allocated by torch in the binding)
 // and submits configured solvers.  A worker thread admits queued solves in
 // arrival order while the arena (first fit) and the slot limit allow and
-// binds each to its own slice of the arena.  Solves that the batched launches
-// can advance (ccpr_pipe_batch_class) are grouped by padded x width: the
+// binds each to its own slice of the arena.  Small solves that the batched
+// launches can advance (ccpr_pipe_batch_class) are grouped by padded x width: the
 // solves of one width share a stream and advance together, one leapfrog step
-// each per batched grid / aux / post launch (up to CCPR_PIPE_BATCH_MAX solves
-// per launch), so a step of many small solves costs three launches instead of
-// three per solve.  Other solves get streams of their own and are fed with
+// each per batched launch (the whole step, or grid, aux and post where a step is
+// not one launch; up to CCPR_PIPE_BATCH_MAX solves per launch), so a step of many
+// small solves costs the launches of one.  Other solves get streams of their own and are fed with
 // chunks of leapfrog steps, round robin, so their kernels overlap on the
 // device.  A finished solve's
 // objective and gradient are copied to its slot's pinned host buffers, its

@@ -270,8 +270,8 @@ int ccpr_launch_fused(const WholeArgs& w, int maxpairs, bool edge, void* stream)
 // waves a CU keeps in flight of it (24, 20 or 16)
 int ccpr_fused_waves(int maxpairs, bool dft);
 // the recorded steps st[0..k) (1 <= k <= CCPR_BATCH_MAX, same nxp, 2 rows per
-// thread, 2 npml <= 256, all of one kind: whole or not) as one batched launch
-// of whole steps, or one batched grid, aux and post launch each
+// thread, 2 npml <= 256, ordinary stores, all of one kind: whole or not) as one
+// batched launch of whole steps, or one batched grid, aux and post launch each
 int ccpr_launch_batch(const BatchStep* st, int k, void* stream);
 // ccpr_launch_aux and ccpr_launch_post_fused as one launch (up to 4 pole pairs,
 // no streaming stores)

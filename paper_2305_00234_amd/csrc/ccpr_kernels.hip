@@ -1418,7 +1418,6 @@ __device__ __forceinline__ int batch_solve(const int* start, int n, int b)
     return s;
 }
 
-template <bool NT>
 __global__ __launch_bounds__(1024) void ccpr_batch_grid_kernel(const BatchArgs B)
 {
     __shared__ float xe[2][3][16];
@@ -1426,7 +1425,7 @@ __global__ __launch_bounds__(1024) void ccpr_batch_grid_kernel(const BatchArgs B
     const int s = batch_solve(B.gstart, B.n, blockIdx.x);
     const StepArgs& a = B.a[s];
     if (*a.halt) return;
-    grid_tile<2, true, NT>(a, (int)blockIdx.x - B.gstart[s], xe, xh);
+    grid_tile<2, true, false>(a, (int)blockIdx.x - B.gstart[s], xe, xh);
 }
 
 template <int DP>
@@ -1439,16 +1438,15 @@ __global__ __launch_bounds__(CCPR_FUSED_THREADS) void ccpr_batch_fused_kernel(co
     fused_tile<DP, false, false>(w, L - k * w.s.nys, k, hs);
 }
 
-template <int PMAX, bool NT>
+template <int PMAX>
 __global__ __launch_bounds__(256) void ccpr_batch_aux_kernel(const BatchArgs B)
 {
     const int s = batch_solve(B.astart, B.n, blockIdx.x);
     const StepArgs& a = B.a[s];
     if (*a.halt) return;
-    aux_cell<PMAX, NT, false, false>(a, ((unsigned)blockIdx.x - (unsigned)B.astart[s]) * 256u + threadIdx.x);
+    aux_cell<PMAX, false, false, false>(a, ((unsigned)blockIdx.x - (unsigned)B.astart[s]) * 256u + threadIdx.x);
 }
 
-template <bool NT>
 __global__ __launch_bounds__(256) void ccpr_batch_post_kernel(const BatchArgs B)
 {
     __shared__ float se[2][256];
@@ -1456,7 +1454,7 @@ __global__ __launch_bounds__(256) void ccpr_batch_post_kernel(const BatchArgs B)
     const StepArgs& a = B.a[s];
     if (*a.halt) return;
     const long long blk = (long long)blockIdx.x - B.pstart[s];
-    if (B.fused[s]) post_fused_block<NT>(a, B.rpb[s], B.nbx[s], B.nmisc[s], B.ntfh[s], blk, se);
+    if (B.fused[s]) post_fused_block<false>(a, B.rpb[s], B.nbx[s], B.nmisc[s], B.ntfh[s], blk, se);
     else post_cell(a, blk * 256 + threadIdx.x, B.nxs[s], B.nmisc[s]);
 }
 
@@ -2149,7 +2147,7 @@ int ccpr_launch_batch(const BatchStep* st, int k, void* stream)
     long long g = 0, x = 0, q = 0;
     for (int s = 0; s < k; ++s) {
         const BatchStep& t = st[s];
-        if (t.whole || t.a.nxp != st[0].a.nxp || t.a.rows != 2 || 2 * t.a.npml > 256)
+        if (t.whole || t.a.nxp != st[0].a.nxp || t.a.rows != 2 || 2 * t.a.npml > 256 || t.a.stream_st)
             return (int)hipErrorInvalidValue;
         B.a[s] = t.a;
         maxp = std::max(maxp, t.maxpairs);
@@ -2172,30 +2170,18 @@ int ccpr_launch_batch(const BatchStep* st, int k, void* stream)
     B.astart[k] = (int)x;
     B.pstart[k] = (int)q;
     hipStream_t hs = (hipStream_t)stream;
-    const bool nt = st[0].a.stream_st != 0;
-    if (g > 0) {
-        if (nt) hipLaunchKernelGGL(ccpr_batch_grid_kernel<true>, dim3((unsigned)g), dim3(st[0].a.nxp), 0, hs, B);
-        else hipLaunchKernelGGL(ccpr_batch_grid_kernel<false>, dim3((unsigned)g), dim3(st[0].a.nxp), 0, hs, B);
-    }
+    if (g > 0) hipLaunchKernelGGL(ccpr_batch_grid_kernel, dim3((unsigned)g), dim3(st[0].a.nxp), 0, hs, B);
     if (x > 0) {
-#define CCPR_BAUX(P)                                                                                     \
-    do {                                                                                                 \
-        if (nt) hipLaunchKernelGGL((ccpr_batch_aux_kernel<P, true>), dim3((unsigned)x), dim3(256), 0, hs, B); \
-        else hipLaunchKernelGGL((ccpr_batch_aux_kernel<P, false>), dim3((unsigned)x), dim3(256), 0, hs, B); \
-    } while (0)
-        if (maxp <= 0) CCPR_BAUX(0);
-        else if (maxp <= 1) CCPR_BAUX(1);
-        else if (maxp <= 2) CCPR_BAUX(2);
-        else if (maxp <= 3) CCPR_BAUX(3);
-        else if (maxp <= 4) CCPR_BAUX(4);
-        else if (maxp <= 6) CCPR_BAUX(6);
-        else CCPR_BAUX(8);
-#undef CCPR_BAUX
+        auto aux = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)x), dim3(256), 0, hs, B); };
+        if (maxp <= 0) aux(ccpr_batch_aux_kernel<0>);
+        else if (maxp <= 1) aux(ccpr_batch_aux_kernel<1>);
+        else if (maxp <= 2) aux(ccpr_batch_aux_kernel<2>);
+        else if (maxp <= 3) aux(ccpr_batch_aux_kernel<3>);
+        else if (maxp <= 4) aux(ccpr_batch_aux_kernel<4>);
+        else if (maxp <= 6) aux(ccpr_batch_aux_kernel<6>);
+        else aux(ccpr_batch_aux_kernel<8>);
     }
-    if (q > 0) {
-        if (nt) hipLaunchKernelGGL(ccpr_batch_post_kernel<true>, dim3((unsigned)q), dim3(256), 0, hs, B);
-        else hipLaunchKernelGGL(ccpr_batch_post_kernel<false>, dim3((unsigned)q), dim3(256), 0, hs, B);
-    }
+    if (q > 0) hipLaunchKernelGGL(ccpr_batch_post_kernel, dim3((unsigned)q), dim3(256), 0, hs, B);
     return (int)hipGetLastError();
 }
 
