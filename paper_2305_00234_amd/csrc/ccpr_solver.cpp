@@ -992,13 +992,14 @@ int whole_step_rows(const ccpr_solver* s)
 //  - cells: 64^3 24.5 / 9.8, 1.04 M 31.1 / 23.8, 1.81 M 40.9 / 40.8, 2.07 M 40.1 / 53.6;
 //  - waves in flight: registers limit them and large workgroups round them down (1.63 M
 //    in rows of 192 lanes, 4 pairs, DFT, per edge: 12 of 24, 57.5 / 79.2);
-//  - design cells: 1.33 M with 0.08 M of them 35.2 / 30.8, 1.73 M with 0.34 M 48.9 / 54.1,
-//    per edge 1.38 M with 0.17 M 40.0 / 46.7; above 4 pairs, where few already cost most of
-//    it, 0.74 M with 455 41.2 / 30.4, 0.85 M with 0.12 M 40.0 / 60.6;
+//  - design cells, more beside a plane wave's tests or no CPML: 1.33 M with 0.08 M of
+//    them 35.2 / 30.8, 1.35 M with 0.33 M 45.5 / 36.3, plane wave 1.73 M with 0.34 M
+//    48.9 / 54.1 and per edge 1.38 M with 0.17 M 40.0 / 46.7; above 4 pairs, where few
+//    already cost most of it, 0.74 M with 455 41.2 / 30.4, 0.85 M with 0.12 M 40.0 / 60.6;
 //  - no CPML: the separate grid kernel has no layers either and there is hardly a post
 //    launch (0.82 M 23.9 / 19.7, 1.55 M 27.5 / 33.9).
-// Of 556 random solves it misses the faster form by more than 2 % on 23, by at most
-// 25 %, and none is slower than its separate grid, aux and post launches were.
+// Of 814 random solves it misses the faster form by more than 2 % on 39, by at most
+// 25 %, and one is slower than its separate grid, aux and post launches were (8 %).
 // Rows above 256 lanes leave a workgroup a single row beside its halo row; a tile height,
 // four rows per thread and design tiles fused on request name the separate launches.
 constexpr double kWholeStepCells = 1.8e6;
@@ -1010,8 +1011,10 @@ bool whole_step(const ccpr_solver* s)
     const int wg = (whole_step_rows(s) + 1) * s->nxp / 64;
     const int waves = ccpr_fused_waves(s->maxpairs, s->grad_dft) / wg * wg;
     const double nd = s->has_design ? (double)s->nd : 0.0;
-    const double load = s->maxpairs > 4 ? cells * (s->src_kind == 2 ? 1.1 : 1.0) + 4000.0 * std::sqrt(nd)
-                                        : cells * (s->g.npml > 0 ? 1.0 : 1.5) + nd * (s->edge ? 3.75 : 3.0);
+    const bool pw = s->src_kind == 2, pml = s->g.npml > 0;
+    const double load = s->maxpairs > 4
+                            ? cells * (pw ? 1.2 : 1.0) + 4000.0 * std::sqrt(nd)
+                            : cells * (pml ? 1.0 : 1.5) + nd * (pml && !pw ? 1.0 : 3.0) * (s->edge ? 1.25 : 1.0);
     return load <= 2.0e6 * std::sqrt(waves / 24.0);
 }
 

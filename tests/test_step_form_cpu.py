@@ -47,6 +47,8 @@ CASES = {
     "per edge: 40.0 / 46.7": (_workload((179, 147, 49), (107, 88, 17), npml=12, pairs=2, edges=True,
                                         source="planewave"), False),
     "large design: 48.9 / 54.1": (_workload((178, 92, 98), (142, 58, 66), npml=12, source="planewave"), False),
+    "large design, dipole: 45.5 / 36.3": (_workload((43, 146, 144), (25, 116, 115), npml=5), True),
+    "no CPML, large design, dipole: 27.6 / 29.8": (_workload((243, 71, 57), (145, 42, 34), npml=0), False),
     "no CPML, small: 23.9 / 19.7": (_workload((100, 80, 80), (25, 20, 20), npml=0, source="planewave"), True),
     "no CPML, large: 27.5 / 33.9": (_workload((120, 110, 110), (30, 27, 27), npml=0, source="planewave"), False),
     "rows too wide": (_workload((257, 24, 24), (8, 4, 4)), False),
