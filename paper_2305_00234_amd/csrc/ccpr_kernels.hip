@@ -638,10 +638,11 @@ __device__ __forceinline__ void design_cell(const StepArgs& a, const long long v
                                             const int kk, const unsigned o, const float* e_in,
                                             const float* d_in)
 {
-    // step data: constant address space inside ccpr_fused_kernel and in the
-    // per-voxel pass of states that fit the last-level cache, a plain pointer
-    // elsewhere (at 320^3 scalar step data took the design pass from 72.8 to
-    // 70.5 us and the grid pass after it from 393.5 to 396.8; per-edge passes
+    // step data: constant address space where the cell's values come from registers
+    // (ccpr_fused_kernel; ccpr_step_des_kernel, whose step at 320^3 went from 740 to
+    // 594 us by it) and in the per-voxel pass of states that fit the last-level cache,
+    // a plain pointer elsewhere (at 320^3 scalar step data took the design pass from
+    // 72.8 to 70.5 us and the grid pass after it from 393.5 to 396.8; per-edge passes
     // got no faster, 20.7 and 21.6 us on 101x85x37 cells)
     constexpr bool CC = REG || (!EDGE && !NT);
     typename std::conditional<CC, ColdRef, const StepCold&>::type c = step_cold<CC>(a);
@@ -1131,11 +1132,12 @@ __device__ __forceinline__ float cpml_new(float& d, float4 cf, float p)
 // are bound by latency: a tile is one plane, its loads are issued at once, no
 // field or CPML load waits for another load (row classes are comparisons, bases
 // come in the argument), step data and coefficients are scalar loads, and the
-// body is short (80 VGPRs with 3 pole pairs, 6 waves per SIMD).  Measured per
-// step on 32^3 / 64^3 / 117^3: separate launches 30.2 / 30.1 / 47.9 us, this
-// 7.8 / 9.9 / 34.1; marching two planes a tile 12.3 / 14.2 / 46.7 (a plane's
-// loads queue behind the stores of the plane before, and 106 VGPRs), two rows
-// a thread with the next plane prefetched 15.0 / 17.6 / 73.9 (200 VGPRs).
+// body is short (78 VGPRs with 3 pole pairs, 6 waves per SIMD).  Measured per step on
+// 32^3 / 64^3 / 117^3, 2 pairs, dipole: separate launches 25.0 / 24.2 / 37.9 us, this
+// 7.0 / 8.8 / 31.8; two planes a tile one after the other 12.3 / 14.2 / 46.7 where this
+// took 7.8 / 9.9 / 34.1 (a plane's loads queue behind the stores of the plane before,
+// and 106 VGPRs), two rows a thread with the next plane prefetched 15.0 / 17.6 / 73.9
+// (200 VGPRs).
 template <int DP, bool DFT, bool EDGE>
 __device__ __forceinline__ void fused_tile(const WholeArgs& w, const int ys, const int k,
                                            float (*hs)[CCPR_FUSED_THREADS])
