@@ -879,6 +879,18 @@ void plan_chunks(ccpr_solver* s)
     s->tiles_host.insert(s->tiles_host.end(), pm.begin(), pm.end());
 }
 
+// Whether the planned grid pass runs as two concurrent launches (where there is a
+// second stream).  It pays for its fork only with enough tiles on both sides, and only
+// where the step streams from memory: two streams' event hops cost 11 us a step,
+// and states that fit the last-level cache lose more by them than the interior
+// tiles gain from a variant without CPML code (us, split / one launch:
+// 150x140x130 60.2 / 55.0, 180x170x160 102.3 / 92.7; above the line 200^3 165 /
+// 173, 240x230x220 203 / 216).
+bool splits(const ccpr_solver* s)
+{
+    return (streams(s) || s->des_on) && s->ntiles_int + s->ntiles_des >= 1024 && s->ntiles_pml >= 128;
+}
+
 ccpr_status upload_cold(ccpr_solver* s, int st)
 {
     plan_chunks(s);
@@ -888,8 +900,7 @@ ccpr_status upload_cold(ccpr_solver* s, int st)
                           hipMemcpyHostToDevice, s->stream));
     // (no second stream on the static workspace: creating one is a resource
     // allocation its callers cannot make)
-    if (s->ntiles_pml > 0 && s->ntiles_int + s->ntiles_des > 0 && !s->stream2 && s->static_dev < 0 &&
-        !s->batched) {
+    if (splits(s) && !s->stream2 && s->static_dev < 0 && !s->batched) {
         HIPCHK(hipStreamCreateWithFlags(&s->stream2, hipStreamNonBlocking));
         s->own_stream2 = true;
     }
@@ -1143,13 +1154,7 @@ ccpr_status launch_step(ccpr_solver* s, StepArgs& A, int st, bool fuse)
     StepArgs Ap = A;
     Ap.tiles = A.tiles + nint + ndt;
     Ap.nblk = npt;
-    // the split pays for its fork only with enough tiles on both sides, and only
-    // where the step streams from memory: two streams' event hops cost 11 us a step,
-    // and states that fit the last-level cache lose more by them than the interior
-    // tiles gain from a variant without CPML code (us, split / one launch:
-    // 150x140x130 60.2 / 55.0, 180x170x160 102.3 / 92.7; above the line 200^3 165 /
-    // 173, 240x230x220 203 / 216)
-    const bool split = s->stream2 && (A.stream_st || s->des_on) && nint + ndt >= 1024 && npt >= 128;
+    const bool split = s->stream2 && splits(s);
     const bool fdes = split && ndt > 0;  // design cells finished in the grid pass
     // interior tiles (with the design tiles unless those run fused)
     StepArgs Ai = A;
